@@ -340,9 +340,10 @@ cwo_status cwo_gs(cwo_ctx* ctx, const cwo_params* p, const float* a1, const floa
  * axis, any value. Errors, checked in this order: p null -> CWO_ERR_INVALID; sizes out of
  * range -> CWO_ERR_UNSUPPORTED; null pointers, misaligned points, npoints < 0, non-finite
  * or non-positive pitch/wavelength, non-finite offsets or oz == 0 -> CWO_ERR_INVALID.
- * Scratch: 32 bytes per point; small holograms also sum up to 16 ranges of points apart, in
- * FP64 (8 or 16 bytes per pixel and range, 64 MiB at most, not used where the budget has no
- * room for it). Stream-ordered. */
+ * Scratch: 32 bytes per point; small holograms of many points also sum up to 16 ranges of
+ * points apart, in FP64, in a buffer of 64 MiB that the first such call allocates and the
+ * context keeps (not used where the budget or the memory has no room for it, nor allocated
+ * while the stream is being captured: one range then). Stream-ordered. */
 typedef struct {
     int32_t nx, ny;        /* hologram pixels */
     double px, py;         /* hologram pitch [m] */

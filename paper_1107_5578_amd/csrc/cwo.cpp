@@ -65,6 +65,7 @@ struct Workspace {
     Buffer fourier;                   // chirp tables and band masks of the shifted forms
     Buffer ework;                     // min/max partials of the scale epilogue
     Buffer pls;                       // FP64 point records of the point-light-source sums
+    Buffer plspart;                   // their partial sums of point ranges (kPlsPartialBytes)
     std::list<FresnelEntry> fresnel;  // most recently used first
     size_t budget = 0;                // 0: unbounded (serving slots are bounded by admission)
     // The one stream that uses this workspace (a serving slot's), or null when calls on
@@ -78,7 +79,8 @@ struct Workspace {
         return owner ? hipStreamSynchronize(owner) : hipDeviceSynchronize();
     }
     void release() {
-        for (Buffer* b : {&scratch, &fwork, &ftab, &gsnum, &rwork, &fourier, &ework, &pls}) {
+        for (Buffer* b : {&scratch, &fwork, &ftab, &gsnum, &rwork, &fourier, &ework, &pls,
+                          &plspart}) {
             if (b->p) (void)hipFree(b->p);
             b->p = nullptr;
             b->bytes = 0;
@@ -274,6 +276,14 @@ void* ensure(cwo_ctx* c, Workspace& ws, Buffer& b, size_t bytes, cwo_status* st)
     b.bytes = bytes;
     ws.total += bytes;
     return b.p;
+}
+
+// Whether the stream records into a graph (where nothing may be allocated).
+bool capturing(hipStream_t s) {
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &cs) == hipSuccess) return cs != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();  // the null stream while another one records
+    return true;
 }
 
 bool finite_pos(double v) { return std::isfinite(v) && v > 0.0; }
@@ -1671,16 +1681,16 @@ cwo_status pls_run(cwo_ctx* c, const cwo_pls_params* p, const float* points, int
     if (st != CWO_OK) return st;
     std::lock_guard<std::mutex> lock(c->mu);
     if ((st = begin(c)) != CWO_OK) return st;
-    // the point records, and partial sums of point ranges where they help and fit the budget
-    const size_t want = cwo::pls_work_bytes(npoints, field, p->nx, p->ny);
-    const size_t least = cwo::pls_point_bytes(npoints);
-    void* work = ensure(c, c->ws, c->ws.pls, want, &st);
-    if (!work && st == CWO_ERR_NOMEM && want > least) {
-        st = CWO_OK;
-        work = ensure(c, c->ws, c->ws.pls, least, &st);
+    void* records = ensure(c, c->ws, c->ws.pls, cwo::pls_point_bytes(npoints), &st);
+    if (!records) return st;
+    // Partial sums of point ranges, where a call wants several: a buffer of its own and of one
+    // size, so that no call replaces memory a captured graph uses (the ranges a call wants
+    // grow with fewer pixels). Without it the call takes one range.
+    void* partial = c->ws.plspart.p;
+    if (!partial && cwo::pls_ranges(npoints, field, p->nx, p->ny) && !capturing(s)) {
+        cwo_status none = CWO_OK;
+        partial = ensure(c, c->ws, c->ws.plspart, cwo::kPlsPartialBytes, &none);
     }
-    if (!work) return st;
-    const size_t have = std::min(c->ws.pls.bytes, want);
     cwo::PlsParams pp;
     pp.nx = p->nx;
     pp.ny = p->ny;
@@ -1697,7 +1707,7 @@ cwo_status pls_run(cwo_ctx* c, const cwo_pls_params* p, const float* points, int
     pp.cre = std::sin(ang) * inv;  // (cos + i sin)/i = sin - i cos
     pp.cim = -std::cos(ang) * inv;
     CWO_HIP(c, timed(c, CWO_STAGE_PLS, s, [&] {
-                return cwo::launch_pls(points, npoints, work, have, out, field, pp, s);
+                return cwo::launch_pls(points, npoints, records, partial, out, field, pp, s);
             }));
     return CWO_OK;
 }

@@ -200,20 +200,23 @@ hipError_t launch_fresnel_planes(double2* work, float2* out, const FresnelPlanes
                                  hipStream_t s);
 
 // Point-light-source sums (hologram or field) over npts points given as float
-// (X, Y, Z, A) records (16-byte aligned). work: pls_work_bytes of memory, or any amount from
-// pls_point_bytes up (partial sums of point ranges are used as far as they fit). The hologram
+// (X, Y, Z, A) records (16-byte aligned). records: pls_point_bytes of memory. partial: memory
+// for the partial sums of point ranges (kPlsPartialBytes; one size for every call, so that no
+// call ever replaces it), or null: one range. The hologram
 // pixel (m, n) sits at ((m - nx/2) px, (n - ny/2) py); point j at (ox + X, oy + Y,
 // oz + Z). The field is multiplied by (cre, cim).
+constexpr size_t kPlsPartialBytes = size_t(64) << 20;
 struct PlsParams {
     int nx, ny;
     double px, py, lam;
     double ox, oy, oz;
     double cre, cim;
 };
-hipError_t launch_pls(const float* points, int npts, void* work, size_t work_bytes, void* out,
+hipError_t launch_pls(const float* points, int npts, void* records, void* partial, void* out,
                       bool field, const PlsParams& pp, hipStream_t s);
 size_t pls_point_bytes(int npts);
-size_t pls_work_bytes(int npts, bool field, int nx, int ny);
+// Whether a call takes several point ranges if it has the memory.
+bool pls_ranges(int npts, bool field, int nx, int ny);
 
 // Independent fields of one geometry in one launch per pass: the row forward pass reads
 // plane k from ins.in[k] into scratch plane k, the row inverse writes plane k to

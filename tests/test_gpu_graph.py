@@ -135,3 +135,41 @@ def test_point_light_source_and_fused_intensity_graph_replay(ctx):
         torch.cuda.synchronize()
         assert torch.equal(holo, ref_h), rep
         assert torch.equal(inten, ref_i), rep
+
+
+@pytest.mark.parametrize("first", [(2048, 2048, 4596, False), (64, 48, 3000, True)])
+def test_point_light_source_graph_survives_smaller_holograms(first):
+    """A hologram sum captured, then eager sums of no more points on other sizes that are summed
+    in other numbers of point ranges (fewer pixels take more of them): the captured records and
+    partial sums stay where they are, so every replay still equals the eager call."""
+    import torch
+    from paper_1107_5578_amd import cwo
+    c = cwo.Context(0)
+    nx, ny, count, field = first
+
+    def run(t, nx, ny, field, out=None):
+        fn = c.pls_field if field else c.pls_cgh
+        return fn(t, nx, ny, 4e-6, 4e-6, 633e-9, 1e-4, 0.0, 0.1, out=out)
+
+    clouds = [torch.from_numpy(W.pls_points(count, 970 + k, half_extent=2e-4)).cuda()
+              for k in range(2)]
+    pts = clouds[0].clone()
+    out = run(pts, nx, ny, field)  # allocates
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        run(pts, nx, ny, field, out)
+    for rep, (sx, sy, n, f) in enumerate([(512, 512, 4000, False), (256, 256, 2000, True),
+                                          (1038, 496, 4596, False), (64, 64, 149, False)]):
+        n = min(n, count)
+        note("graph pls %dx%d, eager %dx%d points=%d field=%s" % (nx, ny, sx, sy, n, f))
+        small = run(clouds[1][:n].contiguous(), sx, sy, f)
+        pts.copy_(clouds[rep % 2])
+        g.replay()
+        torch.cuda.synchronize()
+        ref = run(clouds[rep % 2], nx, ny, field)
+        again = run(clouds[1][:n].contiguous(), sx, sy, f)
+        torch.cuda.synchronize()
+        assert torch.equal(out, ref), rep
+        assert torch.equal(small, again), rep
+    c.close()
