@@ -342,8 +342,8 @@ cwo_status cwo_gs(cwo_ctx* ctx, const cwo_params* p, const float* a1, const floa
  * or non-positive pitch/wavelength, non-finite offsets or oz == 0 -> CWO_ERR_INVALID.
  * Scratch: 32 bytes per point; small holograms of many points also sum up to 16 ranges of
  * points apart, in FP64, in a buffer of 64 MiB that the first such call allocates and the
- * context keeps (not used where the budget or the memory has no room for it, nor allocated
- * while the stream is being captured: one range then). Stream-ordered. */
+ * context keeps (not in a context with a budget, nor where memory is short or while the
+ * stream is being captured: one range then). Stream-ordered. */
 typedef struct {
     int32_t nx, ny;        /* hologram pixels */
     double px, py;         /* hologram pitch [m] */

@@ -1685,9 +1685,10 @@ cwo_status pls_run(cwo_ctx* c, const cwo_pls_params* p, const float* points, int
     if (!records) return st;
     // Partial sums of point ranges, where a call wants several: a buffer of its own and of one
     // size, so that no call replaces memory a captured graph uses (the ranges a call wants
-    // grow with fewer pixels). Without it the call takes one range.
+    // grow with fewer pixels). Without it the call takes one range, as in a context with a
+    // budget, whose room is for what its calls cannot do without.
     void* partial = c->ws.plspart.p;
-    if (!partial && cwo::pls_ranges(npoints, field, p->nx, p->ny) && !capturing(s)) {
+    if (!partial && !c->budget && cwo::pls_ranges(npoints, field, p->nx, p->ny) && !capturing(s)) {
         cwo_status none = CWO_OK;
         partial = ensure(c, c->ws, c->ws.plspart, cwo::kPlsPartialBytes, &none);
     }

@@ -91,3 +91,25 @@ def test_budget_without_room_for_partial_sums():
     _check(b, pts, args, False)
     free.close()
     tight.close()
+
+
+def test_partial_sums_take_no_room_of_a_budget():
+    """A budget that holds a 2048 x 2048 plane and the point records, not partial sums beside
+    them: the plane runs after holograms that would take several ranges, and their sums are
+    one range's."""
+    from paper_1107_5578_amd import cwo
+    n, count, budget = 2048, 2000, 70 << 20
+    ctx = cwo.Context(0, budget)
+    pts = W.pls_points(count, 80, half_extent=2e-4)
+    args = (256, 256, 5e-6, 5e-6, 532e-9, 0.0, 0.0, 0.05)
+    print("[gpu-case] pls then a plane in %d MiB" % (budget >> 20), flush=True)
+    y = _run(ctx, pts, args, True)
+    assert ctx.memory_held() == 32 * count
+    u = torch.from_numpy(W.uniform_random_field(n, 81)).cuda()
+    plane = ctx.asm(u, 8e-6, 8e-6, 532e-9, 0.2)
+    _check(_run(ctx, pts, args, False), pts, args, False)
+    _check(y, pts, args, True)
+    free = cwo.Context(0)
+    assert torch.equal(plane, free.asm(u, 8e-6, 8e-6, 532e-9, 0.2))
+    free.close()
+    ctx.close()
