@@ -230,11 +230,20 @@ hipError_t drain_profile(cwo_ctx* c) {
         if ((call) != hipSuccess) return dev_fail(ctx); \
     } while (0)
 
+// Device memory, or null. The runtime keeps the error of a refused allocation until it is read:
+// left there, the next launch's check would report it.
+void* device_alloc(size_t bytes) {
+    void* p = nullptr;
+    if (hipMalloc(&p, bytes) == hipSuccess) return p;
+    (void)hipGetLastError();
+    return nullptr;
+}
+
 const float2* twiddle_table(cwo_ctx* c, int m, hipStream_t s, cwo_status* st) {
     auto it = c->twiddles.find(m);
     if (it != c->twiddles.end()) return it->second;
-    float2* tw = nullptr;
-    if (hipMalloc(&tw, sizeof(float2) * (size_t)cwo::tw_entries16(m)) != hipSuccess) {
+    float2* tw = (float2*)device_alloc(sizeof(float2) * (size_t)cwo::tw_entries16(m));
+    if (!tw) {
         *st = CWO_ERR_NOMEM;
         return nullptr;
     }
@@ -268,8 +277,8 @@ void* ensure(cwo_ctx* c, Workspace& ws, Buffer& b, size_t bytes, cwo_status* st)
         b.p = nullptr;
         b.bytes = 0;
     }
-    if (hipMalloc(&b.p, bytes) != hipSuccess) {
-        b.p = nullptr;
+    b.p = device_alloc(bytes);
+    if (!b.p) {
         *st = CWO_ERR_NOMEM;
         return nullptr;
     }
@@ -412,7 +421,8 @@ const float2* factor_table(cwo_ctx* c, Workspace& ws, const FresnelKey& key, hip
     }
     FresnelEntry e;
     e.key = key;
-    if (hipMalloc(&e.h, sizeof(float2) * len) != hipSuccess) {
+    e.h = (float2*)device_alloc(sizeof(float2) * len);
+    if (!e.h) {
         *st = CWO_ERR_NOMEM;
         return nullptr;
     }

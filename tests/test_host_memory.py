@@ -1,0 +1,79 @@
+"""Device memory as the library's host side asks for it, on the CPU: libcwo.so bound to a runtime
+that only counts allocations (stub_runtime.cpp), each case in a process of its own. What is
+checked are return codes and bytes; no kernel runs."""
+import os
+import subprocess
+import sys
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+
+PRELUDE = """
+import ctypes, sys
+stub = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)
+stub.stub_held.restype = ctypes.c_size_t
+stub.stub_refuse.argtypes = [ctypes.c_size_t]
+from paper_1107_5578_amd import cwo
+lib = cwo.load()
+PTR = ctypes.c_void_p(1 << 20)  # the caller's device memory: never read here
+
+class Ctx:
+    def __init__(self, budget=0):
+        self.h = ctypes.c_void_p()
+        assert lib.cwo_create(ctypes.byref(self.h), 0, budget) == 0
+    def asm(self, nx, ny, precision="f32"):
+        p = cwo.make_params(nx, ny, 8e-6, precision=precision)
+        return lib.cwo_asm(self.h, ctypes.byref(p), PTR, PTR, None)
+    def pls(self, nx, ny, points, field=False):
+        p = cwo.PlsParams(nx, ny, 4e-6, 4e-6, 633e-9, 0.0, 0.0, 0.1)
+        fn = lib.cwo_pls_field if field else lib.cwo_pls_cgh
+        return fn(self.h, ctypes.byref(p), PTR, points, PTR, None)
+    def gs(self, nx, ny, iterations, precision="f32"):
+        p = cwo.make_params(nx, ny, 8e-6, precision=precision)
+        return lib.cwo_gs(self.h, ctypes.byref(p), PTR, PTR, PTR, iterations, PTR, None)
+    def held(self):
+        n = ctypes.c_size_t()
+        assert lib.cwo_memory_held(self.h, ctypes.byref(n)) == 0
+        return n.value
+"""
+
+
+@pytest.fixture(scope="module")
+def stub(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("stub") / "libstub_runtime.so")
+    subprocess.check_call(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-o", so,
+                           os.path.join(HERE, "stub_runtime.cpp")])
+    return so
+
+
+def run(stub, body):
+    r = subprocess.run([sys.executable, "-c", PRELUDE + body, stub], cwd=ROOT, timeout=120,
+                       capture_output=True, text=True)
+    assert r.returncode == 0, r.stdout + r.stderr
+
+
+@pytest.mark.parametrize("call", ["c.asm(256, 256)", "c.pls(64, 64, 100)", "c.gs(256, 256, 3)"])
+def test_refused_allocation_does_not_end_the_context(stub, call):
+    """A device that is out of memory fails the call, not the calls after it."""
+    run(stub, """
+c = Ctx()
+stub.stub_refuse(1)
+assert %s == cwo.CWO_ERR_NOMEM
+stub.stub_refuse(0)
+assert %s == cwo.CWO_OK
+""" % (call, call))
+
+
+def test_refused_partial_sums(stub):
+    """Without memory for partial sums a point-light-source call takes one range of points."""
+    run(stub, """
+c = Ctx()
+stub.stub_refuse(64 << 20)
+assert c.pls(512, 512, 4000) == cwo.CWO_OK
+assert c.held() == 32 * 4000 == stub.stub_held()
+stub.stub_refuse(0)
+assert c.asm(256, 256) == cwo.CWO_OK
+assert c.pls(512, 512, 4000) == cwo.CWO_OK
+""")
