@@ -14,25 +14,32 @@ namespace cwo {
 // and the constrained field by fwd_scale * (*dyn_fwd) before the forward transform (null
 // dyn pointers count as 1), so FP16 storage stays in range.
 
-// Error partials per row for rows of m points.
-constexpr int gs_partials_per_row(int m) { return m / 16 < 32 ? 1 : m / 16 / 32; }
+// Error partials per row for rows of m points (the same for every kernel of that length: the
+// buffer holds iterations * ny * this).
+constexpr int gs_partials_per_row(int m) { return m / 16 < 64 ? 1 : m / 16 / 64; }
 
-// Error partials of one row of M points: each thread's double summed with those of its row in
-// the same wavefront, W = T/P of them (the row's T threads are T consecutive lanes, or every
-// second lane of two rows side by side: STRIDE 2), by a butterfly of cross-lane exchanges in a
-// fixed order, and stored by the first of them at num[row * P + j / W] (P partials per row,
-// whichever kernel takes rows of that length: W is 32 for rows of 512 and more, and 16 for those
-// of 8192 on the tiled plane). The iteration's error sums them later in a fixed order too, so it stays
-// deterministic; no block barrier is taken here.
-// All lanes of the wavefront call it (store: whether this row exists).
-template <int M, int T, int STRIDE>
-__device__ __forceinline__ void row_partials(double x, double* __restrict__ num, int row, int j,
-                                             bool store) {
+// Error partials of rows of M points, P per row: each thread's double summed with those of W = T/P
+// threads of its row in the same wavefront (the row's T threads are T consecutive lanes, or
+// every second lane of two rows side by side: ROWS 2), by a butterfly of cross-lane exchanges
+// in a fixed order, stored by the first of them at num[row * P + j / W]. Where a wavefront
+// holds 32 threads of each of two rows and W is 64, it sums both rows' in its one partial, the
+// j / 32-th of the pair's 2P. The iteration's error sums them later in a fixed order too, so it
+// stays deterministic; no block barrier is taken here.
+// All lanes of the wavefront call it (store: whether this row exists; row0: the pair's first row).
+template <int M, int T, int ROWS>
+__device__ __forceinline__ void row_partials(double x, double* __restrict__ num, int row0, int c,
+                                             int j, bool store) {
     constexpr int P = gs_partials_per_row(M), W = T / P;
-    static_assert(W <= 32 && P * W == T, "partials of a row");
+    static_assert(W <= 64 && P * W == T, "partials of a row");
+    constexpr bool PAIR = W * ROWS > 64;
 #pragma unroll
-    for (int o = W / 2; o > 0; o >>= 1) x += __shfl_xor(x, o * STRIDE, 64);
-    if (store && (j & (W - 1)) == 0) num[(size_t)row * P + j / W] = x;
+    for (int o = 32; o > 0; o >>= 1)
+        if (PAIR || (o >= ROWS && o < W * ROWS)) x += __shfl_xor(x, o, 64);
+    if constexpr (PAIR) {
+        if (store && c == 0 && (j & 31) == 0) num[(size_t)row0 * P + j / 32] = x;
+    } else {
+        if (store && (j & (W - 1)) == 0) num[(size_t)(row0 + c) * P + j / W] = x;
+    }
 }
 
 // u -> a u/|u| (a where u = 0), u = scale * v; adds (|u| - a)^2 to acc.
@@ -82,7 +89,7 @@ __global__ __launch_bounds__(RowCfg<M>::THREADS) void k_row_gs(
             v[r] = make_float2(0.f, 0.f);  // the padding of the next forward transform
         }
     }
-    if (num) row_partials<M, T, 1>(acc, num, row, j, valid);
+    if (num) row_partials<M, T, 1>(acc, num, row, 0, j, valid);
     if (out) {
         if (valid) {
             float2* orow = out + (size_t)row * nx;
@@ -142,7 +149,7 @@ __global__ __launch_bounds__(TileRowCfg<M>::THREADS) __attribute__((amdgpu_waves
     double acc = 0.0;
 #pragma unroll
     for (int r = 0; r < NL; ++r) v[r] = constrain(v[r], scale, a[r], acc);
-    if (num) row_partials<M, T, C::ROWS>(acc, num, y0 + c, ja, true);
+    if (num) row_partials<M, T, C::ROWS>(acc, num, y0, c, ja, true);
     if (out) {
 #pragma unroll
         for (int r = 0; r < NL; ++r) (out + fy + r * T)[fx] = v[r];
@@ -206,7 +213,7 @@ __global__ __launch_bounds__(MH / 16 * kSplitRows) __attribute__((amdgpu_waves_p
         if (r % 4 == 0) asm volatile("" ::: "memory");
         ev[r] = constrain(ev[r], scale, (amp + fy + r * T)[fx], acc);
     }
-    if (num) row_partials<2 * MH, T, R>(acc, num, y0 + c, ja, true);
+    if (num) row_partials<2 * MH, T, R>(acc, num, y0, c, ja, true);
     if (out) {
 #pragma unroll
         for (int r = 0; r < E; ++r) (out + fy + r * T)[fx] = ev[r];

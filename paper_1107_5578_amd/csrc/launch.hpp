@@ -166,7 +166,8 @@ struct GsScale {
 // storage of gsc.prec, the output of a column pass): inverse row FFT, keep the first nx
 // values scaled as gsc says, replace each value u by a*u/|u| (a where u == 0) with a from
 // amp ([ny][nx] float32), and, if num is not null, store the row's FP64 sum of
-// (|u| - a)^2 as P = gs_partials(mx) partials at num[row*P .. row*P + P-1]. Then either
+// (|u| - a)^2 as P = gs_partials(mx) partials from num[row*P] on (two rows side by side may
+// share their 2P). Then either
 // (out == nullptr) zero-pad and forward row FFT back into spec, or write the constrained
 // field to out ([ny][nx] complex64).
 hipError_t launch_row_gs(void* spec, const float* amp, float2* out, double* num, int nx, int ny,

@@ -77,3 +77,16 @@ stub.stub_refuse(0)
 assert c.asm(256, 256) == cwo.CWO_OK
 assert c.pls(512, 512, 4000) == cwo.CWO_OK
 """)
+
+
+@pytest.mark.parametrize("nx,ny,iterations", [(2048, 2048, 200), (256, 512, 7), (4096, 64, 5)])
+@pytest.mark.parametrize("precision,elem", [("f32", 8), ("f16", 4)])
+def test_gs_scratch(stub, nx, ny, iterations, precision, elem):
+    """The iteration's scratch is the padded spectrum and one error partial per row and 1024
+    padded points, so a budget of that size (FP16: and of the range pre-pass) is enough."""
+    need = elem * ny * 2 * nx + 8 * (iterations * ny * max(1, 2 * nx // 1024) + 512)
+    run(stub, """
+need = %d
+c = Ctx(need if %r == "f32" else need + (64 << 10))
+assert c.gs(%d, %d, %d, %r) == cwo.CWO_OK
+""" % (need, precision, nx, ny, iterations, precision))
