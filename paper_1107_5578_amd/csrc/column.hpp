@@ -263,7 +263,7 @@ __global__ __launch_bounds__(ColCfg<M>::THREADS) __attribute__((amdgpu_waves_per
         v[r] = ld ? ST::dec((base + lay.step(r * T, lt, T))[at]) : make_float2(0.f, 0.f);
     }
     // (the 16 factors of the two-step passes fit beside 4096-point columns only)
-    TwCache<M, ST::kFused, !ST::kFused && M != 4096> twc;
+    TwCache<M, fused_of(ST::kFused, M), !ST::kFused && M != 4096> twc;
     twc.load(j, tw);
     const typename PH::Col hc = hfp.column(col);
     fft<M, FWD, C::COLS, HALF>(v, lds, j, c, twc);

@@ -30,10 +30,10 @@ constexpr int INV = +1;
 // complex64 (FP32), or two FP16 / two BF16 values per complex (rounded to nearest
 // even on the way in). Arithmetic is always FP32.
 //
-// kFused says which of the two transform arithmetics a storage takes (see "transforms"): the
-// fused one for complex64; the two-step one for 16-bit storage, whose roundings turn a
-// last-bit change of an FP32 value into half a unit of 16 bits, so that its stored planes stay
-// the values they were before the fused arithmetic existed.
+// kFused says which of the two transform arithmetics a storage takes: the fused one for
+// complex64 (from kFusedMin points on, see fused_of); the two-step one for 16-bit storage,
+// whose roundings turn a last-bit change of an FP32 value into half a unit of 16 bits, so that
+// its stored planes stay the values they were before the fused arithmetic existed.
 struct StF32 {
     static constexpr bool kFused = true;
     using E = float2;
@@ -211,14 +211,26 @@ __device__ __forceinline__ void dft(float2 (&v)[N]) {
 
 // ---- fused arithmetic ------------------------------------------------------------
 //
-// The transforms are bound by vector issue, so every butterfly is written for fused
-// multiply-adds: (a + w b, a - w b) is a + w b in four of them and a - w b = 2a - (a + w b) in
-// two more. A radix-16 DFT by decimation in time takes its inputs' twiddles w^k along:
-// level l multiplies by w^(8 >> l) W^c, so four levels of eight such butterflies (192
-// instructions) do the DFT and all fifteen input twiddles, against 160 + 60 for a 4 x 4 DFT
-// after multiplying each input, and a thread holds 8 twiddles per pass instead of 15.
+// The transforms are bound by vector issue, so every butterfly (a + w b, a - w b) is written
+// as six fused multiply-adds. A factor is kept as a scale and a ratio: with w = exp(-i t),
+//     w b = cos t (b.x + tan t b.y,  b.y - tan t b.x)      (t up to pi/4, or any t: ratio = tan t)
+//         = sin t (cot t b.x + b.y,  cot t b.y - b.x)      (t from pi/4 on: ratio = cot t),
+// two multiply-adds for the pair in brackets, then one for each component of a + w b and a - w b,
+// which are rounded independently of each other. (With w as it is, a + w b takes four and
+// a - w b = 2a - (a + w b) two more, whose rounding adds to that of the sum: the transform of a
+// padded row of 2048 is then off by 1.25e-7 of its norm, here by 1.11e-7, two-step 1.12e-7.)
+// The bracket is at most |b| over the scale, so its rounding stays relative to |b| for
+// any ratio. A radix-16 DFT by decimation in time takes its inputs' twiddles w^k along: level l
+// multiplies by w^(8 >> l) W^c, so four levels of eight such butterflies (192 instructions) do
+// the DFT and all fifteen input twiddles, against 160 + 60 for a 4 x 4 DFT after multiplying
+// each input, and a thread holds 8 factors per pass instead of 15.
 
-// p - 2 q and p + 2 q forms: s = a + w b, then b = 2a - s, a = s. (wx, wy) is the factor.
+// Whether a transform is fused: below kFusedMin, where a call is bound by its launches, the two-step
+// form is as fast and slightly more exact (a Fresnel plane of 128^2: 2.05e-7, fused
+// 2.10e-7; of 256^2 2.46e-7 and 2.40e-7, of 2048^2 2.86e-7 and 2.65e-7).
+constexpr bool fused_of(bool storage, int m) { return storage && m >= kFusedMin; }
+
+// s = a + w b, b = a - w b, a = s with the factor (w.x, w.y): a factor that is not a table's.
 __device__ __forceinline__ void bf_w(float2& a, float2& b, float wx, float wy) {
     const float sx = __fmaf_rn(-wy, b.y, __fmaf_rn(wx, b.x, a.x));
     const float sy = __fmaf_rn(wy, b.x, __fmaf_rn(wx, b.y, a.y));
@@ -226,14 +238,17 @@ __device__ __forceinline__ void bf_w(float2& a, float2& b, float wx, float wy) {
     a = make_float2(sx, sy);
 }
 
-// Butterfly with the factor w (a table entry exp(-i t)) for DIR = FWD, conj(w) for INV,
-// times exp(DIR*i*pi/2) if ROT.
-template <int DIR, bool ROT>
-__device__ __forceinline__ void bf_tw(float2& a, float2& b, float2 w) {
-    if constexpr (DIR == FWD && !ROT) bf_w(a, b, w.x, w.y);
-    else if constexpr (DIR == FWD) bf_w(a, b, w.y, -w.x);
-    else if constexpr (!ROT) bf_w(a, b, w.x, -w.y);
-    else bf_w(a, b, w.y, w.x);
+// The same with the factor exp(-i t) as scale and ratio (sr.x, sr.y) for DIR = FWD, its
+// conjugate for INV, times exp(DIR*i*pi/2) if ROT. COT: scale sin t and ratio cot t, else cos t and
+// tan t.
+template <int DIR, bool COT, bool ROT>
+__device__ __forceinline__ void bf_sr(float2& a, float2& b, float2 sr) {
+    constexpr float d = DIR == FWD ? 1.0f : -1.0f;
+    float2 p = COT ? make_float2(__fmaf_rn(sr.y, b.x, d * b.y), __fmaf_rn(sr.y, b.y, -d * b.x))
+                   : make_float2(__fmaf_rn(d * sr.y, b.y, b.x), __fmaf_rn(-d * sr.y, b.x, b.y));
+    if constexpr (ROT) p = rot90<DIR>(p);
+    b = make_float2(__fmaf_rn(-sr.x, p.x, a.x), __fmaf_rn(-sr.x, p.y, a.y));
+    a = make_float2(__fmaf_rn(sr.x, p.x, a.x), __fmaf_rn(sr.x, p.y, a.y));
 }
 
 // Butterfly with the constant factor exp(DIR*2*pi*i*m/R), R <= 16.
@@ -246,13 +261,15 @@ __device__ __forceinline__ void bf_const(float2& a, float2& b) {
         b = csub(a, t);
         a = cadd(a, t);
     } else {
+        constexpr bool cot = m16 == 3 || m16 == 5;
         constexpr double ctab[8] = {1.0, 0.92387953251128675613, 0.70710678118654752440,
                                     0.38268343236508977173, 0.0, -0.38268343236508977173,
                                     -0.70710678118654752440, -0.92387953251128675613};
-        constexpr double stab[8] = {0.0, 0.38268343236508977173, 0.70710678118654752440,
-                                    0.92387953251128675613, 1.0, 0.92387953251128675613,
-                                    0.70710678118654752440, 0.38268343236508977173};
-        bf_w(a, b, (float)ctab[m16], DIR == FWD ? -(float)stab[m16] : (float)stab[m16]);
+        constexpr double c = cot ? ctab[m16 - 4 < 0 ? 4 - m16 : m16 - 4] : ctab[m16];  // the scale
+        constexpr double s = cot ? ctab[m16] : ctab[m16 < 4 ? 4 - m16 : m16 - 4];
+        constexpr float ratio = (float)(s / c);
+        constexpr float scale = (float)((c + s * ratio) / (1.0 + (double)ratio * ratio));
+        bf_sr<DIR, cot, false>(a, b, make_float2(scale, ratio));
     }
 }
 
@@ -285,29 +302,33 @@ __device__ __forceinline__ void dft_const(float2 (&u)[R]) {
     }
 }
 
-// Radix-16 DFT of u[k] w^k (w^-k for INV); u[p] = X_bitrev(p). t holds the table entries
-// w^8, w^4, w^2, w^2 W8, w, w W8, w W16, w W16^3.
+// Radix-16 DFT of u[k] w^k (w^-k for INV); u[p] = X_bitrev(p). t holds the table's factors
+// w^8, w^4, w^2, w^2 W8, w, w W8, w W16, w W16^3 (those of an angle from pi/4 on, numbers 3, 5 and
+// 7, with the ratio cot).
 template <int DIR>
 __device__ __forceinline__ void dft16_tw(float2 (&u)[16], const float2 (&t)[8]) {
 #pragma unroll
-    for (int k = 0; k < 8; ++k) bf_tw<DIR, false>(u[k], u[k + 8], t[0]);
+    for (int k = 0; k < 8; ++k) bf_sr<DIR, false, false>(u[k], u[k + 8], t[0]);
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-        bf_tw<DIR, false>(u[k], u[k + 4], t[1]);
-        bf_tw<DIR, true>(u[k + 8], u[k + 12], t[1]);
+        bf_sr<DIR, false, false>(u[k], u[k + 4], t[1]);
+        bf_sr<DIR, false, true>(u[k + 8], u[k + 12], t[1]);
     }
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
-        bf_tw<DIR, false>(u[k], u[k + 2], t[2]);
-        bf_tw<DIR, true>(u[k + 4], u[k + 6], t[2]);
-        bf_tw<DIR, false>(u[k + 8], u[k + 10], t[3]);
-        bf_tw<DIR, true>(u[k + 12], u[k + 14], t[3]);
+        bf_sr<DIR, false, false>(u[k], u[k + 2], t[2]);
+        bf_sr<DIR, false, true>(u[k + 4], u[k + 6], t[2]);
+        bf_sr<DIR, true, false>(u[k + 8], u[k + 10], t[3]);
+        bf_sr<DIR, true, true>(u[k + 12], u[k + 14], t[3]);
     }
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-        bf_tw<DIR, false>(u[4 * g], u[4 * g + 1], t[4 + g]);
-        bf_tw<DIR, true>(u[4 * g + 2], u[4 * g + 3], t[4 + g]);
-    }
+    bf_sr<DIR, false, false>(u[0], u[1], t[4]);
+    bf_sr<DIR, false, true>(u[2], u[3], t[4]);
+    bf_sr<DIR, true, false>(u[4], u[5], t[5]);
+    bf_sr<DIR, true, true>(u[6], u[7], t[5]);
+    bf_sr<DIR, false, false>(u[8], u[9], t[6]);
+    bf_sr<DIR, false, true>(u[10], u[11], t[6]);
+    bf_sr<DIR, true, false>(u[12], u[13], t[7]);
+    bf_sr<DIR, true, true>(u[14], u[15], t[7]);
 }
 
 // ---- pass plan and twiddles -----------------------------------------------------
@@ -329,7 +350,7 @@ struct Plan {
 // forward and the inverse transform, or (LAZY) read from the table before each pass, where the
 // registers are wanted for other values (they are read before the exchange, while the
 // transform's own values are in LDS).
-template <int M, bool FUSED = true, bool LAZY = false>
+template <int M, bool FUSED = fused_of(true, M), bool LAZY = false>
 struct TwCache {
     using PL = Plan<M>;
     static constexpr int F = FUSED ? 8 : 16;  // factors per pass
@@ -362,11 +383,11 @@ struct TwCache {
     }
     // tw: the table of length M
     __device__ __forceinline__ void load(int jt, const float2* __restrict__ tw) {
-        load_at(jt, tw + (FUSED ? M : tw_entries(M)));
+        load_at(jt, tw + (FUSED ? M : tw_at16(M)));
     }
     // twm: the table of length 2M
     __device__ __forceinline__ void load_half(int jt, const float2* __restrict__ twm) {
-        load_at(jt, twm + (FUSED ? 2 * M : tw_entries(2 * M)) + F * tw_pass_k(2 * M));
+        load_at(jt, twm + (FUSED ? 2 * M : tw_at16(2 * M)) + F * tw_pass_k(2 * M));
     }
 };
 

@@ -71,7 +71,7 @@ __global__ __launch_bounds__(RowCfg<M>::THREADS) void k_row_gs(
     const float* arow = amp + (size_t)(valid ? row : 0) * nx;
     float2* my_lds = lds + sub * lds_elems<M>();
     if (dyn_inv) scale *= *dyn_inv;
-    TwCache<M, ST::kFused, !ST::kFused> twc;
+    TwCache<M, fused_of(ST::kFused, M), !ST::kFused> twc;
     twc.load(j, tw);
     float2 v[E];
 #pragma unroll
@@ -135,7 +135,7 @@ __global__ __launch_bounds__(TileRowCfg<M>::THREADS) __attribute__((amdgpu_waves
 #pragma unroll
     for (int r = 0; r < E; ++r)
         v[r] = ST::dec((spec + lay.tile_step(y0, r * (T / kTileW), T / kTileW))[at]);
-    TwCache<M, ST::kFused, true> twc;
+    TwCache<M, fused_of(ST::kFused, M), true> twc;
     twc.load(j, tw);
     fft<M, INV, C::ROWS>(v, lds, j, c, twc);
     // opaque copies of j: addresses and twiddles are made where they are used, not held

@@ -79,21 +79,22 @@ hipError_t launch_range_scale(const float2* in, size_t n, float* work, hipStream
 hipError_t launch_range_scale(const float* in, size_t n, float* work, hipStream_t s);
 
 constexpr int ilog2c(int x) { return x <= 1 ? 0 : 1 + ilog2c(x / 2); }
+constexpr int kFusedMin = 512;  // shortest transform in fused arithmetic (see fft_device.hpp)
 // The twiddle table of length M: exp(-2 pi i k/M), k < M, then for each pass p >= 1 of a
-// length-M transform (and of a length-M/2 one) the 8 factors of each k < Ns, w = W_{16 Ns}^k,
-// in pairs: entry (q, k) of a pass holds factors 2q and 2q + 1 in 16 bytes, so that a
-// wavefront reads consecutive entries. tw_entries(m) ends here; the table a context keeps goes
-// on with the 16 factors w^0 .. w^15 that the transforms of 16-bit planes take (see kFused),
-// laid out the same: tw_entries16(m) in all.
+// length-M transform (and of a length-M/2 one) the 8 factors of each k < Ns, w = W_{16 Ns}^k, as
+// scale and ratio (see bf_sr), in pairs: entry (q, k) of a pass holds factors 2q and 2q + 1 in
+// 16 bytes, so that a wavefront reads consecutive entries. From tw_at16(m) on come the 16 factors
+// w^0 .. w^15 of the two-step arithmetic, laid out the same: tw_entries16(m) in all. Complex64
+// transforms of kFusedMin points and more do without them: tw_entries(m).
 constexpr int tw_pass_k(int m) {  // sum of Ns over the passes of a length-m transform
     const int bits = ilog2c(m), first = (bits % 4) == 0 ? 4 : bits % 4;
     int n = 0;
     for (int ns = 1 << first; ns < m; ns <<= 4) n += ns;
     return n;
 }
-constexpr int tw_pass_entries(int m) { return 8 * tw_pass_k(m); }
-constexpr int tw_entries(int m) { return m + 8 * (tw_pass_k(m) + tw_pass_k(m / 2)); }
-constexpr int tw_entries16(int m) { return tw_entries(m) + 16 * (tw_pass_k(m) + tw_pass_k(m / 2)); }
+constexpr int tw_at16(int m) { return m + 8 * (tw_pass_k(m) + tw_pass_k(m / 2)); }
+constexpr int tw_entries16(int m) { return tw_at16(m) + 16 * (tw_pass_k(m) + tw_pass_k(m / 2)); }
+constexpr int tw_entries(int m) { return m < kFusedMin ? tw_entries16(m) : tw_at16(m); }
 // Fills the first n values of the table of length m (tw_entries(m) or tw_entries16(m)).
 hipError_t launch_twiddles(float2* tw, int m, int n, hipStream_t s);
 

@@ -44,7 +44,7 @@ __global__ __launch_bounds__(RowCfg<M>::THREADS) void k_row_fwd(IN ins,
     const int row = blockIdx.x * C::RPB + sub;
     const bool valid = row < ny;
     const float2* src = ins(blockIdx.y) + (size_t)(valid ? row : 0) * nx;
-    TwCache<M, ST::kFused> twc;
+    TwCache<M, fused_of(ST::kFused, M)> twc;
     twc.load(j, tw);
     float2 v[E];
 #pragma unroll
@@ -87,7 +87,7 @@ __global__ __launch_bounds__(RowCfg<M>::THREADS) void k_row_fwd_pf(IN ins,
     const float f = sc.dyn ? sc.in * *sc.dyn : sc.in;
     const int rows = ny * batch;
     const int groups = (rows + C::RPB - 1) / C::RPB;
-    TwCache<M, ST::kFused> twc;
+    TwCache<M, fused_of(ST::kFused, M)> twc;
     twc.load(j, tw);
     auto load = [&](int g, float2 (&d)[NL]) {
         const int w = g * C::RPB + sub;
@@ -138,7 +138,7 @@ __global__ __launch_bounds__(RowCfg<M>::THREADS) void k_row_inv(
     const int row = blockIdx.x * C::RPB + sub;
     const bool valid = row < ny;
     const typename ST::E* src = in + blockIdx.y * in_plane + (size_t)(valid ? row : 0) * M;
-    TwCache<M, ST::kFused> twc;
+    TwCache<M, fused_of(ST::kFused, M)> twc;
     twc.load(j, tw);
     float2 v[E];
 #pragma unroll
@@ -165,7 +165,7 @@ __global__ __launch_bounds__(RowCfg<M>::THREADS) void k_row_inv_pf(
     if (dyn_inv) scale *= *dyn_inv;
     const int rows = ny * batch;
     const int groups = (rows + C::RPB - 1) / C::RPB;
-    TwCache<M, ST::kFused> twc;
+    TwCache<M, fused_of(ST::kFused, M)> twc;
     twc.load(j, tw);
     using SE = typename ST::E;
     auto load = [&](int g, SE (&d)[E]) {
@@ -219,7 +219,7 @@ __global__ __launch_bounds__(TileRowCfg<M>::THREADS) __attribute__((amdgpu_waves
 #pragma unroll
     for (int r = 0; r < NL; ++r) v[r] = (src + r * T)[at];
     const float f = sc.dyn ? sc.in * *sc.dyn : sc.in;
-    TwCache<M, ST::kFused> twc;
+    TwCache<M, fused_of(ST::kFused, M)> twc;
     twc.load(j, tw);
 #pragma unroll
     for (int r = 0; r < NL; ++r) {
@@ -254,7 +254,7 @@ __global__ __launch_bounds__(TileRowCfg<M>::THREADS) __attribute__((amdgpu_waves
 #pragma unroll
     for (int r = 0; r < E; ++r)
         v[r] = ST::dec((src + lay.tile_step(y0, r * (T / kTileW), T / kTileW))[from]);
-    TwCache<M, ST::kFused> twc;
+    TwCache<M, fused_of(ST::kFused, M)> twc;
     twc.load(j, tw);
     fft<M, INV, C::ROWS>(v, lds, j, c, twc);
     const size_t base = (size_t)(y0 + c) * nx + j;
@@ -299,7 +299,20 @@ __global__ void k_twiddles(float2* tw, int m, int n) {
         a = f == 0 ? 8 : f == 1 ? 4 : f < 4 ? 2 : 1;
         b = f == 3 ? 2 : f == 5 ? 2 : f == 6 ? 1 : f == 7 ? 3 : 0;
     }
-    *dst = unit_root((double)(a * k + b * ns), 16.0 * ns);
+    if (per == 16) {
+        *dst = unit_root((double)(a * k + b * ns), 16.0 * ns);
+        return;
+    }
+    // scale and ratio of exp(-i t): the ratio tan t (cot t from pi/4 on, factors 3, 5 and 7) is
+    // rounded first, the scale such that scale and scale * ratio are nearest to cos t and sin t.
+    // Only w^8 reaches t = pi/2, at k = ns/2: a scale of 2^-28 puts its factor 2^-28 off -i and
+    // leaves room for values up to 2^99.
+    const bool cot = f == 3 || f == 5 || f == 7;
+    double sn, cs;
+    sincospi(2.0 * (double)(a * k + b * ns) / (16.0 * ns), &sn, &cs);
+    const double u = cot ? sn : fabs(cs) < 0x1p-28 ? 0x1p-28 : cs, v = cot ? cs : sn;
+    const float ratio = (float)(v / u);
+    *dst = make_float2((float)((u + v * ratio) / (1.0 + (double)ratio * ratio)), ratio);
 }
 
 // ---- host launchers ------------------------------------------------------------

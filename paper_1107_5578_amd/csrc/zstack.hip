@@ -18,7 +18,8 @@ namespace cwo {
 //
 // Fast form (every bin s <= 0.05): K = 1 - sqrt(1 - s) = s/2 + T(s) from the same
 // series as AsmHFast; minus the phase of plane z is zl*K - zl revolutions, reduced to [0, 1)
-// in FP64. 16-bit storage (see kFused) keeps reduce(zl) - reduce(zl*K), subtracted in FP32.
+// in FP64. 16-bit storage and short columns (see fused_of) keep reduce(zl) - reduce(zl*K),
+// subtracted in FP32 (more exact there: 2.53e-7 of a plane's norm at 128^2, else 2.55e-7).
 // Exact form: Q = sqrt(1 - s) in FP64 (Q < 0 marks an evanescent bin, s > 1, decided with
 // the reference's operations); the phase is zl*Q.
 struct AsmZFast {
@@ -154,7 +155,7 @@ __global__ __launch_bounds__(ZColCfg<M>::THREADS) __attribute__((amdgpu_waves_pe
     asm volatile("" : "+v"(col0));
     const bool active = col0 < mx;
     const int col = active ? col0 : 0;
-    TwCache<M, ST::kFused> twc;
+    TwCache<M, fused_of(ST::kFused, M)> twc;
     twc.load(j, tw);
     float2 v[E];
     zcol_forward<M, HALF, ST>(spec + col, ny, mx, j, c, active, v, lds, twc);
@@ -167,7 +168,7 @@ __global__ __launch_bounds__(ZColCfg<M>::THREADS) __attribute__((amdgpu_waves_pe
                                  const double zl = zs.zl[k];
                                  const double zr = rint(zl) - zl;
                                  return [&kb, &zs, zl, zr](auto rc) {
-                                     return zs.h.template at<ST::kFused>(kb[decltype(rc)::value], zl, zr);
+                                     return zs.h.template at<fused_of(ST::kFused, M)>(kb[decltype(rc)::value], zl, zr);
                                  };
                              });
 }
@@ -185,7 +186,7 @@ __global__ __launch_bounds__(ZColCfg<M>::THREADS) __attribute__((amdgpu_waves_pe
     asm volatile("" : "+v"(col0));
     const bool active = col0 < mx;
     const int col = active ? col0 : 0;
-    TwCache<M, ST::kFused> twc;
+    TwCache<M, fused_of(ST::kFused, M)> twc;
     twc.load(j, tw);
     float2 v[E];
     zcol_forward<M, HALF, ST>(spec + col, ny, mx, j, c, active, v, lds, twc);
@@ -230,7 +231,7 @@ __global__ __launch_bounds__(ZRowCfg<M>::THREADS) __attribute__((amdgpu_waves_pe
         if constexpr (T >= 4) v[r] = ST::dec((base + (size_t)(r * T) * ny)[at]);
         else v[r] = ST::dec(base[place(j + r * T)]);
     }
-    TwCache<M, ST::kFused, !ST::kFused> twc;
+    TwCache<M, fused_of(ST::kFused, M), !ST::kFused> twc;
     twc.load(j, tw);
     fft<M, INV, C::COLS>(v, lds, j, c, twc);
     if (!active) return;  // after the last exchange: no barrier follows
