@@ -49,13 +49,14 @@ struct AsmH {
 // Fast form, used when every bin has s = (lambda fx)^2 + (lambda fy)^2 <= 0.05 (so none is
 // evanescent): with x = s/2, 1 - sqrt(1 - 2x) = x + x^2/2 + x^3/2 + 5x^4/8 + ..., so the phase
 // in revolutions is zl - zl*(x + ...), evaluated in FP64 with its sign turned, zl in the
-// coefficients and the constant reduced on the host, and reduced to [0, 1) by the exact FP64
-// fractional part before it is rounded to FP32. The series to n = 9 has a truncation error
-// below 3e-12 relative for s <= 0.05, and the launcher takes NT = 4
-// where zl times the rest of the series is below 2^-28 revolution on the whole grid. The
-// hardware sine and cosine take revolutions. One series for the whole phase costs a bin six
-// FP64 multiply-adds; reducing column, row and remainder terms separately took eight FP64 and
-// three FP32 operations.
+// coefficients and the constant reduced on the host, and reduced to [-1/2, 1/2] in FP64 before
+// it is rounded to FP32: the phases of z and -z are then rounded alike, so that a propagation
+// there and back cancels them (the ping-pong iteration of 512^2: 2.4e-7 off, with the fraction in
+// [0, 1), one operation less, 4.4e-7). The series to n = 9 has a truncation error below 3e-12
+// relative for s <= 0.05, and the launcher takes NT = 4 where zl times the rest of the series is
+// below 2^-28 revolution on the whole grid. The hardware sine and cosine take revolutions. One
+// series for the whole phase costs a bin six FP64 multiply-adds; reducing column, row and
+// remainder terms separately took eight FP64 and three FP32 operations.
 template <int NT>
 struct AsmHFastN {
     static_assert(NT == 4 || NT == 9, "series length");
@@ -105,7 +106,8 @@ struct AsmHFastN {
         return fma(q, x, k0);
     }
     __device__ __forceinline__ float2 operator()(const Col& c, const Row& rw) const {
-        const float r = (float)__builtin_amdgcn_fract(turns(c, rw));
+        const double t = turns(c, rw);
+        const float r = (float)(t - rint(t));
         return make_float2(__builtin_amdgcn_cosf(r), -__builtin_amdgcn_sinf(r));
     }
 };

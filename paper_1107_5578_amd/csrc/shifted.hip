@@ -98,7 +98,8 @@ struct ShiftedFast {
         return Row{b.row(c.c, j, off, soff), -sh.oy * ((double)(j + soff) * dfy), (mask + mx + off)[j]};
     }
     __device__ __forceinline__ float2 operator()(const Col& c, const Row& r) const {
-        const float u = (float)__builtin_amdgcn_fract(b.turns(c.c, r.r) + (c.t + r.t));
+        const double t = b.turns(c.c, r.r) + (c.t + r.t);
+        const float u = (float)(t - rint(t));
         const float m = c.m * r.m;
         return make_float2(m * __builtin_amdgcn_cosf(u), -m * __builtin_amdgcn_sinf(u));
     }

@@ -8,6 +8,7 @@ import pytest
 import torch
 
 from oracle import diffraction as D
+from oracle import gs as G
 from oracle import shifted_asm as SA
 from oracle import shifted_fresnel as SF
 from paper_1107_5578_amd import workloads as W
@@ -31,6 +32,7 @@ BOUNDS = {
     ('zstack', 1024, 512): 2.47e-07,
     ('zfresnel', 64, 64): 1.88e-07, ('zfresnel', 128, 128): 2.15e-07,
     ('zfresnel', 256, 256): 2.45e-07, ('zfresnel', 1024, 512): 2.56e-07,
+    ('gs', 64, 64): 2.85e-07, ('gs', 256, 256): 2.14e-07, ('gs', 512, 512): 2.19e-07,
 }
 
 
@@ -63,6 +65,18 @@ def _results(ctx, op, nx, ny, seed):
         z = [0.05, 0.11, 0.2]
         return (ctx.zstack(t, z, 8e-6, None, LAM, kind="fresnel")[1],
                 D.fresnel(u, 8e-6, None, LAM, z[1]))
+    if op == "gs":  # a smooth beam and target, three iterations
+        y, x = np.mgrid[0:ny, 0:nx] / float(ny)
+        a1 = (0.9 + 0.1 * np.cos(7 * x + seed) * np.cos(5 * y)).astype(np.float32)
+        a2 = (0.75 + 0.25 * np.cos(4 * x) * np.cos(9 * y + seed)).astype(np.float32)
+        u = (a1 * np.exp(0.3j * np.cos(6 * x - 8 * y))).astype(np.complex64)
+        v = torch.from_numpy(u).cuda()
+        ctx.gs(v, torch.from_numpy(a1).cuda(), torch.from_numpy(a2).cuda(), 8e-6, None, LAM, 0.08,
+               iterations=3)
+        r = u
+        for _ in range(3):
+            r = G.iteration(r, a1, a2, 8e-6, LAM, 0.08)[0]
+        return v, r
     raise ValueError(op)
 
 
