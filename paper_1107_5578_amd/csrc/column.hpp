@@ -225,6 +225,22 @@ __device__ __forceinline__ int buffer_plane(const PlaneList<HF>& t, int pl) {
     return t.idx[pl];
 }
 
+// Waves per SIMD the column kernels are compiled for: four (128 VGPRs), where the fast forms
+// spill nothing below columns of 8192. The exact forms hold FP64 values beside the column and spill 8 to
+// 145 registers there; with two waves none, which is faster except for complex64 columns of 4096
+// at full length, whose blocks of 512 threads then have a CU each. Four and two waves, planes of
+// the exact form: 512^2 complex64 20.6 and 19.6 us, 2048^2 98.6 and 119, 4096^2 517 and 507; FP16
+// 1024^2 42.3 and 39.4, 2048^2 142 and 126, 4096^2 595 and 493; shifted 4096^2 686 and 561, FP16
+// 725 and 539.
+template <class HF>
+constexpr bool kExactForm = false;
+template <>
+inline constexpr bool kExactForm<AsmH> = true;
+template <class HF, class ST, int M, bool SPLIT>
+constexpr int col_waves() {
+    return kExactForm<HF> && !(M == 4096 && !SPLIT && std::is_same_v<ST, StF32>) ? 2 : 4;
+}
+
 // Transfer function objects give column(p) for a column and row(column, j, off, soff) for its
 // row j + off, soff being off as a signed frequency index offset (off or off - My).
 
@@ -236,7 +252,7 @@ __device__ __forceinline__ int buffer_plane(const PlaneList<HF>& t, int pl) {
 // none) multiplies the stored values; scaling by a power of two commutes exactly with
 // the inverse transform, so this equals scaling the transfer function.
 template <int M, bool HALF, class HF, class ST, class LAY>
-__global__ __launch_bounds__(ColCfg<M>::THREADS) __attribute__((amdgpu_waves_per_eu(ColCfg<M>::WAVES_PER_EU))) void k_col(typename ST::E* __restrict__ buf,
+__global__ __launch_bounds__(ColCfg<M>::THREADS) __attribute__((amdgpu_waves_per_eu(col_waves<HF, ST, M, false>()))) void k_col(typename ST::E* __restrict__ buf,
                                                               int ny, int mx, int batch,
                                                               size_t plane, HF hf, float hscale,
                                                               const float2* __restrict__ tw,
@@ -294,7 +310,7 @@ __global__ __launch_bounds__(ColCfg<M>::THREADS) __attribute__((amdgpu_waves_per
 // work and one pass's twiddles) and a block to the LDS of one transform per column.
 // twm: the length-M table.
 template <int MH, class HF, class ST, class LAY>
-__global__ __launch_bounds__(MH / 8) __attribute__((amdgpu_waves_per_eu(4))) void k_col_split(
+__global__ __launch_bounds__(MH / 8) __attribute__((amdgpu_waves_per_eu(col_waves<HF, ST, 2 * MH, true>()))) void k_col_split(
     typename ST::E* __restrict__ buf, int ny, int mx, int batch, size_t plane, HF hf, float hscale,
     const float2* __restrict__ twm, LAY lay) {
     constexpr int E = kE, T = MH / E, C = 2;

@@ -71,6 +71,9 @@ struct ShiftedH {
     }
 };
 
+template <class B>
+inline constexpr bool kExactForm<ShiftedH<B>> = true;
+
 // Fast phase form with the shift folded into its phase: the column and the row add their
 // -ox fx (reduced) and -oy fy to the negated phase in FP64, so no extra sine or cosine is
 // taken; the band limits are 0/1 factors.
