@@ -9,6 +9,7 @@ import torch
 
 from oracle import diffraction as D
 from oracle import gs as G
+from oracle import pls as PL
 from oracle import shifted_asm as SA
 from oracle import shifted_fresnel as SF
 from paper_1107_5578_amd import workloads as W
@@ -33,6 +34,14 @@ BOUNDS = {
     ('zfresnel', 64, 64): 1.88e-07, ('zfresnel', 128, 128): 2.15e-07,
     ('zfresnel', 256, 256): 2.45e-07, ('zfresnel', 1024, 512): 2.56e-07,
     ('gs', 64, 64): 2.85e-07, ('gs', 256, 256): 2.14e-07, ('gs', 512, 512): 2.19e-07,
+    ('pls150', 300, 200): 2.40e-07,
+    ('pls256', 300, 200): 3.02e-07,
+    ('pls260', 300, 200): 3.05e-07,
+    ('pls300', 300, 200): 3.25e-07,
+    ('pls383', 300, 200): 3.65e-07,
+    ('pls384', 300, 200): 3.66e-07,
+    ('pls600', 300, 200): 3.95e-07,
+    ('pls2000', 300, 200): 4.15e-07,
 }
 
 
@@ -77,7 +86,9 @@ def _results(ctx, op, nx, ny, seed):
         for _ in range(3):
             r = G.iteration(r, a1, a2, 8e-6, LAM, 0.08)[0]
         return v, r
-    raise ValueError(op)
+    pts = W.pls_points(int(op[3:]), seed, half_extent=4e-3)
+    a = (nx, ny, 4e-6, 4e-6, 633e-9, 10e-3, -2e-3, 0.2)
+    return ctx.pls_cgh(torch.from_numpy(pts).cuda(), *a), PL.cgh(pts, *a)
 
 
 def mean_error(op, nx, ny):
