@@ -1588,7 +1588,7 @@ cwo_status cwo_fresnel_fourier(cwo_ctx* c, const cwo_params* p, const void* in, 
     // 1/i is minus a quarter revolution; a negative z turns the sign (the amplitude's)
     const double t = p->z / p->wavelength;
     fp.t0 = t - std::nearbyint(t) - 0.25;
-    fp.amp = (float)(p->dx * p->dy / (p->wavelength * p->z));
+    fp.amp = p->dx * p->dy / (p->wavelength * p->z);
     CWO_HIP(c, timed(c, CWO_STAGE_ROW_FWD, s, [&] {
                 return cwo::launch_fresnel_fourier((const float2*)in, (float2*)out, fp, twx, twy, s);
             }));

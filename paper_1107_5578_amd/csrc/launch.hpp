@@ -294,8 +294,7 @@ struct FourierPlan {
     double dx2, dy2;  // destination pitch lambda z/(N d) [m]
     double inv2lz;    // 1/(2 lambda z)
     // the constant dx dy exp(i k z)/(i lambda z) = amp exp(2 pi i t0)
-    float amp;
-    double t0;
+    double amp, t0;
 };
 // in, out: complex64 [ny][nx] (may alias); twx, twy: twiddle tables of length nx and ny.
 hipError_t launch_fresnel_fourier(const float2* in, float2* out, const FourierPlan& fp,

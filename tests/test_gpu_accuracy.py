@@ -8,6 +8,7 @@ import pytest
 import torch
 
 from oracle import diffraction as D
+from oracle import fresnel_fourier as FF
 from oracle import gs as G
 from oracle import pls as PL
 from oracle import shifted_asm as SA
@@ -33,6 +34,8 @@ BOUNDS = {
     ('zstack', 1024, 512): 2.47e-07,
     ('zfresnel', 64, 64): 1.88e-07, ('zfresnel', 128, 128): 2.15e-07,
     ('zfresnel', 256, 256): 2.45e-07, ('zfresnel', 1024, 512): 2.56e-07,
+    ('fourier', 16, 16): 1.09e-07, ('fourier', 64, 64): 1.37e-07, ('fourier', 256, 256): 1.56e-07,
+    ('fourier', 512, 1024): 1.73e-07, ('fourier', 4096, 64): 1.68e-07,
     ('gs', 64, 64): 2.85e-07, ('gs', 256, 256): 2.14e-07, ('gs', 512, 512): 2.19e-07,
     ('pls150', 300, 200): 2.40e-07,
     ('pls256', 300, 200): 3.02e-07,
@@ -67,6 +70,8 @@ def _results(ctx, op, nx, ny, seed):
     if op == "sfresnel":
         a = (8e-6, 8e-6, 12e-6, 12e-6, LAM, 0.5, 0.0, 0.0, 2e-3, -1e-3)
         return ctx.fresnel_shifted(t, *a), SF.propagate(u, *a)
+    if op == "fourier":
+        return ctx.fresnel_fourier(t, 8e-6, None, LAM, 0.5), FF.propagate(u, 8e-6, None, LAM, 0.5)
     if op == "zstack":
         z = [0.05, 0.11, 0.2]
         return (ctx.zstack(t, z, 8e-6, None, LAM)[1], D.asm(u, 8e-6, None, LAM, z[1]))
