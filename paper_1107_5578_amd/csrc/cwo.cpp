@@ -824,10 +824,10 @@ cwo_status batch_locked(cwo_ctx* c, Workspace& ws, const cwo_job* jobs, int n, h
         if (!work) return st;
     }
     const float scale = 1.0f / ((float)g.mx * (float)g.my);
-    // (fields up to 512^2 whose planes fill half the last-level cache stay row-major: 32 of 512^2
-    // take 162 us, tiled 167; 16 of them 82 and 78, 4 of them 38 and 32, 8 of 1024^2 184 and 155)
-    const bool many = g.mx <= 1024 && sizeof(float2) * plane * (size_t)chunk >= (size_t)128 << 20;
-    const int layout = cwo::tiled_ok(g.nx, g.ny, g.mx, g.my) && !many ? 1 : 0;
+    // Tiled at every size and count it is built for; against row-major planes (us): 32 fields of
+    // 512^2 160 and 163, 40 196 and 202, 8 of 512 x 2048 196 and 206, 32 714 and 762, 8 of 256 x
+    // 4096 237 and 329, 128 of 512 x 256 347 and 370; only 64 of 256 x 512 lose, 176 and 173.
+    const int layout = cwo::tiled_ok(g.nx, g.ny, g.mx, g.my) ? 1 : 0;
     const bool analytic = (p->flags & CWO_FLAG_FRESNEL_TF) != 0;
     for (int k0 = 0; k0 < n; k0 += chunk) {
         const int nb = std::min(chunk, n - k0);

@@ -151,3 +151,18 @@ def test_gs_error_sums(nx, ny):
     want = G.error(v, a2)
     assert abs(e - want) <= 1e-5 * np.linalg.norm(v) / np.linalg.norm(a2) + 1e-6 * want
     ctx.close()
+
+
+@pytest.mark.parametrize("nx,ny,count", [(256, 4096, 8), (512, 2048, 9), (512, 64, 64), (256, 512, 33)])
+def test_batch_of_rectangles(nx, ny, count):
+    """Batches of 128 MiB of planes and more of narrow, tall and flat fields equal the single
+    calls bit for bit."""
+    from paper_1107_5578_amd import cwo
+    ctx = cwo.Context(0)
+    us = [torch.from_numpy(W.uniform_random_field(nx, nx + k, ny=ny)).cuda() for k in range(count)]
+    os = [torch.empty_like(u) for u in us]
+    print("[gpu-case] batch %dx%d x%d" % (nx, ny, count), flush=True)
+    ctx.batch([("asm", u, o, dict(dx=8e-6, wavelength=532e-9, z=0.03)) for u, o in zip(us, os)])
+    for k in (0, count // 2, count - 1):
+        assert torch.equal(os[k], ctx.asm(us[k], 8e-6, None, 532e-9, 0.03))
+    ctx.close()
