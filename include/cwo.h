@@ -404,7 +404,8 @@ cwo_status cwo_release(cwo_ctx* ctx, uint64_t ticket);
 cwo_status cwo_drain(cwo_ctx* ctx);
 /* Bytes of device memory the context holds now: twiddle tables, the synchronous calls'
  * workspace and every serving slot's scratch and Fresnel factors (not the caller's fields).
- * Between the scheduler's admissions it stays within the budget. */
+ * Between the scheduler's admissions it stays within the budget but for the factors the
+ * transforms derive from the twiddles (0.3 MiB at most), which an admission does not charge. */
 cwo_status cwo_memory_held(cwo_ctx* ctx, size_t* bytes);
 
 /* Validate a parameter set for `kind` without touching any device: the same checks the

@@ -128,6 +128,7 @@ struct cwo_ctx {
     cwo_status sticky = CWO_OK;
     std::map<int, float2*> twiddles;  // FP32 exp(-2 pi i k / M) per M
     std::atomic<size_t> twiddle_bytes{0};
+    std::atomic<size_t> factor_bytes{0};  // of them the passes' factors
     Workspace ws;                     // workspace of the synchronous calls
     // serving; lock order: qmu before mu
     std::mutex qmu;  // tickets, queue, admission state
@@ -255,6 +256,7 @@ const float2* twiddle_table(cwo_ctx* c, int m, hipStream_t s, cwo_status* st) {
         return nullptr;
     }
     c->twiddles[m] = tw;
+    c->factor_bytes += sizeof(float2) * (size_t)(cwo::tw_entries16(m) - m);
     c->twiddle_bytes += sizeof(float2) * (size_t)cwo::tw_entries16(m);
     return tw;
 }
@@ -1063,6 +1065,10 @@ size_t held_bytes(cwo_ctx* c) {
     return h;
 }
 
+// What an admission charges of it: of the transform tables the M roots of unity alone, so that
+// requests that fit beside those are admitted (the passes' factors are 0.3 MiB at most).
+size_t charged_bytes(cwo_ctx* c) { return held_bytes(c) - c->factor_bytes.load(); }
+
 // Requests of one serving batch that do not touch each other's buffers are independent;
 // such a batch is reordered (stably) so that requests of one geometry sit next to each
 // other, those on one field first among them: run_jobs then runs them as shared-launch
@@ -1165,7 +1171,7 @@ void serve_loop(cwo_ctx* c) {
                 group_batch(grouped, gids);
                 const WsNeed need = jobs_need(c, grouped.data(), (int)grouped.size());
                 auto fits = [&] {
-                    return !c->budget || c->reserved + io + io_bytes(&tk.job.p) + held_bytes(c) +
+                    return !c->budget || c->reserved + io + io_bytes(&tk.job.p) + charged_bytes(c) +
                                                  growth(sl.ws, need) <=
                                              c->budget;
                 };

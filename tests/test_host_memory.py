@@ -90,3 +90,20 @@ need = %d
 c = Ctx(need if %r == "f32" else need + (64 << 10))
 assert c.gs(%d, %d, %d, %r) == cwo.CWO_OK
 """ % (need, precision, nx, ny, iterations, precision))
+
+
+@pytest.mark.parametrize("n", [64, 256, 4096])
+def test_served_requests_in_a_tight_budget(stub, n):
+    """A budget of one request's footprint and the roots of unity of its transforms serves one
+    request after the other."""
+    run(stub, """
+n = %d
+c = Ctx(16 * n * n + 8 * n * 2 * n + 8 * 2 * n)
+for k in range(3):
+    job = cwo.Job(cwo.make_params(n, n, 8e-6, kind=cwo.ANGULAR), PTR, PTR)
+    t, state = ctypes.c_uint64(), ctypes.c_int32()
+    assert lib.cwo_submit(c.h, ctypes.byref(job), ctypes.byref(t)) == 0
+    assert lib.cwo_drain(c.h) == 0
+    assert lib.cwo_poll(c.h, t.value, ctypes.byref(state)) == 0
+    assert state.value == cwo.DONE, k
+""" % n)
