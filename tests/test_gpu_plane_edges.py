@@ -153,6 +153,30 @@ def test_gs_error_sums(nx, ny):
     ctx.close()
 
 
+@pytest.mark.parametrize("nx,ny", [(4096, 16), (4096, 64), (2048, 32), (256, 16), (128, 64)])
+def test_gs_field_and_errors(nx, ny):
+    """Three iterations of the row kernel's forms (split rows of 8192, whole tiled rows, row-major
+    rows) against the oracle: the field and every E_k. Six propagations, each within 5e-7 of its
+    norm, and constraints that enlarge an error by the ratio of amplitudes (a few) stay below 1e-5."""
+    from oracle import gs as G
+    from paper_1107_5578_amd import cwo
+    ctx = cwo.Context(0)
+    y, x = np.mgrid[0:ny, 0:nx].astype(np.float64)
+    a1 = (0.9 + 0.1 * np.cos(2e-3 * x + 0.3 * y)).astype(np.float32)
+    a2 = (0.75 + 0.25 * np.cos(5e-3 * x - 0.2 * y)).astype(np.float32)
+    u = (a1 * np.exp(0.3j * np.cos(4e-3 * x + 0.1 * y))).astype(np.complex64)
+    print("[gpu-case] gs field %dx%d" % (nx, ny), flush=True)
+    v = torch.from_numpy(u).cuda()
+    e = ctx.gs(v, torch.from_numpy(a1).cuda(), torch.from_numpy(a2).cuda(), 8e-6, None, 532e-9, 0.01,
+               iterations=3).cpu().numpy()
+    r = u
+    for k in range(3):
+        r, want = G.iteration(r, a1, a2, 8e-6, 532e-9, 0.01)
+        assert abs(e[k] - want) <= 1e-5
+    assert D.rel_l2(v.cpu().numpy(), r) <= 1e-5
+    ctx.close()
+
+
 @pytest.mark.parametrize("nx,ny,count", [(256, 4096, 8), (512, 2048, 9), (512, 64, 64), (256, 512, 33)])
 def test_batch_of_rectangles(nx, ny, count):
     """Batches of 128 MiB of planes and more of narrow, tall and flat fields equal the single
@@ -165,4 +189,18 @@ def test_batch_of_rectangles(nx, ny, count):
     ctx.batch([("asm", u, o, dict(dx=8e-6, wavelength=532e-9, z=0.03)) for u, o in zip(us, os)])
     for k in (0, count // 2, count - 1):
         assert torch.equal(os[k], ctx.asm(us[k], 8e-6, None, 532e-9, 0.03))
+    ctx.close()
+
+
+@pytest.mark.parametrize("nx,ny", [(16, 16), (128, 64), (16, 256), (256, 16)])
+def test_noalloc_short_transforms(nx, ny):
+    """Transforms below 512 points take their factors from the end of the tables, which the
+    static scratch holds as well."""
+    from paper_1107_5578_amd import cwo
+    ctx = cwo.Context(0)
+    t = torch.from_numpy(W.uniform_random_field(nx, nx + 17 * ny, ny=ny)).cuda()
+    out = torch.empty_like(t)
+    print("[gpu-case] noalloc %dx%d" % (nx, ny), flush=True)
+    ctx.asm_noalloc(t, 8e-6, None, 532e-9, 0.03, out=out)
+    assert torch.equal(out, ctx.asm(t, 8e-6, None, 532e-9, 0.03))
     ctx.close()

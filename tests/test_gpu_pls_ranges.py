@@ -113,3 +113,19 @@ def test_partial_sums_take_no_room_of_a_budget():
     assert torch.equal(plane, free.asm(u, 8e-6, 8e-6, 532e-9, 0.2))
     free.close()
     ctx.close()
+
+
+@pytest.mark.parametrize("nx,ny,count", [(64, 48, 4000), (512, 512, 4000), (700, 300, 11646)])
+@pytest.mark.parametrize("field", [False, True])
+def test_point_ranges_are_taken(nx, ny, count, field):
+    """Small holograms of many points allocate the partial sums (64 MiB, once): several ranges
+    were summed, and the result is the oracle's."""
+    from paper_1107_5578_amd import cwo
+    ctx = cwo.Context(0)
+    pts = W.pls_points(count, 90, half_extent=2e-4)
+    args = (nx, ny, 5e-6, 6e-6, 532e-9, 0.0, 0.0, 0.05)
+    print("[gpu-case] pls ranges %dx%d points=%d field=%s" % (nx, ny, count, field), flush=True)
+    y = _run(ctx, pts, args, field)
+    assert ctx.memory_held() == 32 * count + (64 << 20)
+    _check(y, pts, args, field)
+    ctx.close()
