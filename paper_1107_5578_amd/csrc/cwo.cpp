@@ -1706,7 +1706,12 @@ cwo_status pls_run(cwo_ctx* c, const cwo_pls_params* p, const float* points, int
     void* partial = c->ws.plspart.p;
     if (!partial && !c->budget && cwo::pls_ranges(npoints, field, p->nx, p->ny) && !capturing(s)) {
         cwo_status none = CWO_OK;
+        // (relaxed: the records may be there already, and an allocation that the caller need not
+        // expect would end a capture that another stream of the process is in)
+        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+        (void)hipThreadExchangeStreamCaptureMode(&mode);
         partial = ensure(c, c->ws, c->ws.plspart, cwo::kPlsPartialBytes, &none);
+        (void)hipThreadExchangeStreamCaptureMode(&mode);
     }
     cwo::PlsParams pp;
     pp.nx = p->nx;

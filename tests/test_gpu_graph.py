@@ -173,3 +173,37 @@ def test_point_light_source_graph_survives_smaller_holograms(first):
         assert torch.equal(out, ref), rep
         assert torch.equal(small, again), rep
     c.close()
+
+
+def test_first_partial_sums_beside_a_capture():
+    """A plane is captured while a hologram of few pixels, the first to want partial sums, is
+    summed on another stream: the graph is whole and the hologram right."""
+    import torch
+    from paper_1107_5578_amd import cwo
+    note("pls beside a capture")
+    planes, sums = cwo.Context(0), cwo.Context(0)
+    src = fields(256, 3, 980)
+    u, out = src[0].clone(), torch.empty_like(src[0])
+    planes.asm(u, 8e-6, 8e-6, 532e-9, 0.2, out=out)
+    pts = torch.from_numpy(W.pls_points(4000, 981, half_extent=2e-4)).cuda()
+    args = (4e-6, 4e-6, 633e-9, 1e-4, 0.0, 0.1)
+    sums.pls_cgh(pts[:100].contiguous(), 2048, 2048, *args)  # records for fewer points
+    sums.pls_cgh(pts, 2048, 2048, *args)                     # one range
+    held = sums.memory_held()
+    holo = torch.empty((256, 256), device="cuda")
+    side = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        planes.asm(u, 8e-6, 8e-6, 532e-9, 0.2, out=out)
+        sums.pls_cgh(pts, 256, 256, *args, out=holo, stream=side)
+    torch.cuda.synchronize()
+    assert sums.memory_held() == held + (64 << 20)
+    for rep, f in enumerate(src):
+        u.copy_(f)
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, planes.asm(f, 8e-6, 8e-6, 532e-9, 0.2)), rep
+    assert torch.equal(holo, sums.pls_cgh(pts, 256, 256, *args))
+    planes.close()
+    sums.close()

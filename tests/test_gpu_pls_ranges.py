@@ -115,7 +115,7 @@ def test_partial_sums_take_no_room_of_a_budget():
     ctx.close()
 
 
-@pytest.mark.parametrize("nx,ny,count", [(64, 48, 4000), (512, 512, 4000), (700, 300, 11646)])
+@pytest.mark.parametrize("nx,ny,count", [(64, 48, 4000), (200, 150, 3000), (512, 64, 2500)])
 @pytest.mark.parametrize("field", [False, True])
 def test_point_ranges_are_taken(nx, ny, count, field):
     """Small holograms of many points allocate the partial sums (64 MiB, once): several ranges

@@ -107,3 +107,17 @@ for k in range(3):
     assert lib.cwo_poll(c.h, t.value, ctypes.byref(state)) == 0
     assert state.value == cwo.DONE, k
 """ % n)
+
+
+def test_partial_sums_while_another_stream_records(stub):
+    """A call whose records fit may run while another stream of the process records a graph: its
+    first partial sums are allocated without ending that capture."""
+    run(stub, """
+c = Ctx()
+assert c.pls(2048, 2048, 4596) == cwo.CWO_OK
+assert c.held() == 32 * 4596
+stub.stub_record(1)
+assert c.pls(512, 512, 4000) == cwo.CWO_OK
+assert stub.stub_unsafe_allocations() == 0
+assert c.held() == 32 * 4596 + (64 << 20)
+""")
