@@ -335,7 +335,7 @@ cwo_status cwo_gs(cwo_ctx* ctx, const cwo_params* p, const float* a1, const floa
  * points: device float [npoints][4] records (X, Y, Z, A), 16-byte aligned, read only;
  * npoints == 0 writes zeros. out: device [ny][nx], float (hologram) or complex64 (field),
  * caller-owned. Each term's phase is evaluated and reduced modulo one revolution in FP64 and
- * its remainder rounded to FP32 (from 384 points on to 2^-23 revolution), its cosine/sine are
+ * its remainder rounded to FP32 (from 264 points on to 2^-23 revolution), its cosine/sine are
  * FP32; partial sums over 128 points are FP32, the total FP64. Points
  * with z_j == 0 give non-finite values (not checked on the device). Sizes: 1..16384 per
  * axis, any value. Errors, checked in this order: p null -> CWO_ERR_INVALID; sizes out of
