@@ -39,7 +39,8 @@
  *
  * Errors: every call returns a cwo_status. Parameters are validated before anything is
  * launched. A device error makes the context return CWO_ERR_DEVICE from then on.
- * NaN or Inf inside field data is not checked and propagates.
+ * NaN or Inf inside field data is not checked and propagates. Transforms of 512 points and
+ * more hold values of up to 2^99 (6e29) on their way, their largest outputs included.
  */
 #ifndef CWO_H
 #define CWO_H

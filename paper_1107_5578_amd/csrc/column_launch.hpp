@@ -6,8 +6,8 @@
 
 namespace cwo {
 
-// On the tiled plane a padded column of 8192 runs by default as two transforms of 4096 (one
-// column per block), shorter ones as one transform per column.
+// On the tiled plane a padded column of 8192 runs by default as two transforms of 4096, shorter
+// ones as one transform per column; two columns per block in both.
 // ALT launchers (single planes, where the autotuner may pick the column form) also build the
 // other form at 4096 and 8192: col_form 1 full length, 2 split.
 template <class HF, class ST, bool ALT = false>

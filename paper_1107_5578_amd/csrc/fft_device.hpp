@@ -218,15 +218,16 @@ __device__ __forceinline__ void dft(float2 (&v)[N]) {
 // two multiply-adds for the pair in brackets, then one for each component of a + w b and a - w b,
 // which are rounded independently of each other. (With w as it is, a + w b takes four and
 // a - w b = 2a - (a + w b) two more, whose rounding adds to that of the sum: the transform of a
-// padded row of 2048 is then off by 1.25e-7 of its norm, here by 1.11e-7, two-step 1.12e-7.)
+// padded row of 2048 is then off by 1.25e-7 of its norm, here by 1.11e-7, two-step 1.12e-7,
+// evaluated on the CPU.)
 // The bracket is at most |b| over the scale, so its rounding stays relative to |b| for
 // any ratio. A radix-16 DFT by decimation in time takes its inputs' twiddles w^k along: level l
 // multiplies by w^(8 >> l) W^c, so four levels of eight such butterflies (192 instructions) do
 // the DFT and all fifteen input twiddles, against 160 + 60 for a 4 x 4 DFT after multiplying
 // each input, and a thread holds 8 factors per pass instead of 15.
 
-// Whether a transform is fused: below kFusedMin, where a call is bound by its launches, the two-step
-// form is as fast and slightly more exact (a Fresnel plane of 128^2: 2.05e-7, fused
+// Whether a transform is fused: below kFusedMin, where a call is bound by its launches, the
+// two-step form is as fast and slightly more exact (a Fresnel plane of 128^2: 2.05e-7, fused
 // 2.10e-7; of 256^2 2.46e-7 and 2.40e-7, of 2048^2 2.86e-7 and 2.65e-7).
 constexpr bool fused_of(bool storage, int m) { return storage && m >= kFusedMin; }
 
@@ -239,8 +240,8 @@ __device__ __forceinline__ void bf_w(float2& a, float2& b, float wx, float wy) {
 }
 
 // The same with the factor exp(-i t) as scale and ratio (sr.x, sr.y) for DIR = FWD, its
-// conjugate for INV, times exp(DIR*i*pi/2) if ROT. COT: scale sin t and ratio cot t, else cos t and
-// tan t.
+// conjugate for INV, times exp(DIR*i*pi/2) if ROT. COT: scale sin t and ratio cot t, else cos t
+// and tan t.
 template <int DIR, bool COT, bool ROT>
 __device__ __forceinline__ void bf_sr(float2& a, float2& b, float2 sr) {
     constexpr float d = DIR == FWD ? 1.0f : -1.0f;

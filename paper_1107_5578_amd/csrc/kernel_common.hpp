@@ -103,11 +103,12 @@ struct TileRowCfg {
 };
 
 // Column pass: COLS adjacent columns per block in consecutive lanes, one column (16 values)
-// per thread, so that a wavefront moves 8*COLS contiguous bytes per row and every thread
-// keeps to 128 VGPRs: four waves per SIMD, where two columns and 30 twiddles per thread had
-// two. Blocks are small (256 or 512 threads) so that several per CU are in different phases:
-// at M = 4096 1024 threads (4 columns) took 58 us where 2 columns take 44-48 and one 45; at
-// M = 512 two columns (one wave per block) spread a 256^2 field over 256 blocks.
+// per thread, so that a wavefront moves 8*COLS contiguous bytes per row and a thread with a
+// fast transfer function keeps to 128 VGPRs: four waves per SIMD (see col_waves), where two
+// columns and 30 twiddles per thread had two. Blocks are small (256 or 512 threads) so that
+// several per CU are in different phases: at M = 4096 1024 threads (4 columns) took 58 us where 2
+// columns take 44-48 and one 45; at M = 512 two columns (one wave per block) spread a 256^2 field
+// over 256 blocks.
 template <int M, int COLS_ = (M >= 2048 ? 2 : M >= 1024 ? 4 : M >= 512 ? 2 : 4096 / M)>
 struct ColCfg {
     static constexpr int T = M / 16;

@@ -152,7 +152,7 @@ static hipError_t launch_shifted_t(void* buf, int ny, int my, int mx, const HF& 
         using C = ColCfg<MM>;
         const int items = (mx + C::COLS - 1) / C::COLS;
         if (half && layout == 1) {
-            if constexpr (MM == 8192)  // two transforms of 4096 per column, one per block
+            if constexpr (MM == 8192)  // two transforms of 4096 per column
                 launch_kernel((k_col_split<MM / 2, HF, ST, LayTile<typename ST::E>>), dim3(mx / 2), dim3(MM / 16),
                                    0, s, (SE*)buf, ny, mx, 1, (size_t)0, hf, hscale, tw,
                                    LayTile<typename ST::E>{ny});
